@@ -92,6 +92,15 @@ void launch_restrict(const LaunchCtx&, Grid fine, Grid coarse, int transfer, Vec
 template <typename T>
 void launch_prolong_add(const LaunchCtx&, Grid coarse, Grid fine, int transfer, Vec<T> e, Vec<T> u);
 
+// The Krylov basis of a GMRES(3) step (hm_gram.hpp): v_0 = r,
+// v_{j+1} = (sigma A - theta_j) v_j, theta in units of sigma A; pivot_min: squared
+// relative distance from its predecessors below which a column counts as dependent.
+struct GmBasis {
+    double sigma = 0.0;
+    double theta[3] = {0.0, 0.0, 0.0};
+    double pivot_min = 0.0;
+};
+
 // The update pass of a coarse level's last post-smoothing GMRES step, left to
 // the pass that reads its result (the coarse grid correction of the next finer
 // level): u = base + sum_i cu_i v_i over v = r, W_0, W_1 with base = uin (or u
@@ -106,7 +115,7 @@ struct DeferredUpdate {
     Vec<T> uin{nullptr, 0};  // the iterate the step started from, when not u
     const double* part = nullptr;  // Gram partial sums of the step's powers pass
     int nblk = 0;
-    double sigma = 0.0, theta = 0.0;
+    GmBasis basis{};
 };
 
 // A coarse grid correction to fold into the next smoothing step: u += P e with

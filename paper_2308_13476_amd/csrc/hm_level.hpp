@@ -375,7 +375,7 @@ __device__ __forceinline__ void apply_from_tile(const Op& op, int rpt, const Til
 template <typename Op, typename T, typename XGet, typename F>
 __device__ __forceinline__ void for_nodes_applied(const Op& op, int rpt, XGet&& xget, F&& f) {
     for_nodes_applied_pre<Op, T>(op, rpt, xget, Ident{}, [](long long) { return NoVals{}; },
-                                 [&](int i, int j, long long p, NoVals, cplx<T> x, cplx<T> ax) { f(i, j, p, x, ax); });
+                                 [&](int i, int j, long long p, NoVals, cplx<T> x, auto ax) { f(i, j, p, x, ax); });
 }
 
 // Dynamic LDS bytes of an operator kernel launched with geometry (by, rpt).

@@ -426,6 +426,48 @@ __device__ __forceinline__ cplx<T> held_sum(const cplx<T> (&c)[N], At&& at) {
     return y;
 }
 
+// The same sum with less rounding (the Krylov vectors of FP32 steps, hm_gram.hpp): runs
+// of kWideRun products are added up in FP32, the runs in FP64. Against sums in FP32 it
+// costs 22.6 us (20.9) on 512 intervals, radius 2, and 20.8 (19.6), 9.9 (9.8), 8.2 (8.0) on
+// 256, 128 and 64, radius 3. All in FP64, four conversions an entry, 26.6, 83 (spills),
+// 11.5 and 9.9 for errors a fifth smaller; runs of a stencil's row are a tenth off.
+constexpr int kWideRun = 3;
+struct WideSum {
+    cplx<double> y{0.0, 0.0};
+    cplx<float> s{0.0f, 0.0f};
+    // entry d of n (compile-time after unrolling)
+    __device__ __forceinline__ void add(int d, int n, cplx<float> c, cplx<float> x) {
+        s = d % kWideRun == 0 ? cplx<float>{fmaf(c.re, x.re, -(c.im * x.im)), fmaf(c.re, x.im, c.im * x.re)} : cfma(s, c, x);
+        if (d % kWideRun == kWideRun - 1 || d == n - 1) y = y + cast<double>(s);
+    }
+};
+template <int N, int CH, typename At>
+__device__ __forceinline__ cplx<double> held_sum_wide(const cplx<float> (&c)[N], At&& at) {
+    constexpr int NB = (N + CH - 1) / CH;
+    cplx<float> v[2][CH];
+    WideSum t;
+#pragma unroll
+    for (int d = 0; d < CH && d < N; ++d) v[0][d] = at(d);
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+#pragma unroll
+        for (int d = 0; d < CH; ++d)
+            if ((b + 1) * CH + d < N) v[(b + 1) & 1][d] = at((b + 1) * CH + d);
+        stay_here(t.s);
+        stay_here(t.y);
+#pragma unroll
+        for (int d = 0; d < CH; ++d)
+            if (b * CH + d < N) t.add(b * CH + d, N, c[b * CH + d], v[b & 1][d]);
+        stay_here(t.s);
+        stay_here(t.y);
+    }
+    return t.y;
+}
+template <int N, int CH, typename At>
+__device__ __forceinline__ cplx<double> held_sum_wide(const cplx<double> (&c)[N], At&& at) {
+    return held_sum<double, N, CH>(c, at);
+}
+
 template <typename Op>
 struct is_stencil {
     static constexpr bool value = false;
@@ -445,6 +487,34 @@ template <typename T, int R>
 struct op_radius<StencilOp<T, R>> {
     static constexpr int value = R;
 };
+// A stored FP32 stencil applied as in held_sum_wide.
+template <int R>
+struct WideStencil : StencilOp<float, R> {};
+template <int R>
+struct op_radius<WideStencil<R>> {
+    static constexpr int value = R;
+};
+template <int R>
+struct is_stencil<WideStencil<R>> {
+    static constexpr bool value = true;
+    static constexpr int radius = R;
+};
+template <int R>
+__device__ __forceinline__ cplx<double> apply_tile_pre(const WideStencil<R>& op, const cplx<float>* lds, int li, int,
+                                                       int, long long p, NoVals) {
+    constexpr int TW = Tile<R>::TW;
+    constexpr int D = 2 * R + 1;
+    WideSum t;
+#pragma unroll
+    for (int d = 0; d < D * D; ++d)
+        t.add(d, D * D, op.at(d / D - R, d % D - R, p), lds[li + (d / D - R) * TW + d % D - R]);
+    return t.y;
+}
+template <typename Op>
+__device__ __forceinline__ const Op& widened(const Op& op) { return op; }
+template <int R>
+__device__ __forceinline__ WideStencil<R> widened(const StencilOp<float, R>& op) { return WideStencil<R>{op}; }
+
 template <typename T, bool B>
 struct op_radius<ProductOp<T, B>> {
     static constexpr int value = 3;  // coarse halo that the fine stages need

@@ -11,9 +11,10 @@
 // into registers once per smoothing step (once per visit with Jacobi sweeps), an
 // application reads LDS only, in batches that overlap the multiply-adds
 // (held_sum), and GMRES(3) steps take one block reduction each (hm_gram.hpp).
-// Levels 16, 8 and 4 of a V(1,1) cycle: 31.5 us in FP32 and 38 us in FP64 in a
-// replayed cycle (41.7 and 49.7 us with a whole stencil per thread and reads the
-// compiler waits for two by two), W(1,1) in FP32 42.6 us (58).
+// Levels 16, 8 and 4 of a V(1,1) cycle on 1024 intervals: 32.7 us in FP32 and 46.6 us in
+// FP64, W(1,1) in FP32 on 512 intervals 44.0 us (41.7 and 49.7 on the first grid, 58 on
+// the second with a whole stencil per thread and reads the compiler waits for two by
+// two).
 #include "hm_gram.hpp"
 
 namespace hm {
@@ -103,8 +104,10 @@ struct THeld {
         c[0] = cplx<T>{T(0), T(0)};
         if (part == 0) c[0] = *reinterpret_cast<const cplx<T>*>(base + (long long)R * pb + mid);
     }
-    // (A x)_q at the LDS index ln of the node, in both of its lanes.
-    __device__ __forceinline__ cplx<T> apply(const TLv<T>& L, int ln, const cplx<T>* x) const {
+    // (A x)_q at the LDS index ln of the node, in both of its lanes (wide: FP64, summed as
+    // in held_sum_wide).
+    template <bool kWide = false>
+    __device__ __forceinline__ auto apply(const TLv<T>& L, int ln, const cplx<T>* x) const {
         const int part = held_part();
         const cplx<T>* rows = x + ln + (part ? 1 : -R) * L.lp - R;
         const cplx<T>* mid = x + ln + (part ? 1 : -R);
@@ -112,8 +115,14 @@ struct THeld {
         auto at = [&](int d) {
             return d == 0 ? *first : (d - 1 < R * D ? rows[(d - 1) / D * L.lp + (d - 1) % D] : mid[d - 1 - R * D]);
         };
-        const cplx<T> y = held_sum<T, kTaps, sizeof(T) == 4 ? 9 : 4>(c, at);
-        return {half_sum(y.re), half_sum(y.im)};
+        constexpr int CH = sizeof(T) == 4 ? 9 : 4;
+        if constexpr (kWide) {
+            const cplx<double> y = held_sum_wide<kTaps, CH>(c, at);
+            return cplx<double>{half_sum(y.re), half_sum(y.im)};
+        } else {
+            const cplx<T> y = held_sum<T, kTaps, CH>(c, at);
+            return cplx<T>{half_sum(y.re), half_sum(y.im)};
+        }
     }
 };
 // Larger levels: threads take nodes in turns, coefficients from memory.
@@ -164,6 +173,31 @@ __device__ __forceinline__ void tail_apply(const TLv<T>& L, int, const TBig<R>&,
         const int q = thread_here() + v * kTailThreads;
         if (q < L.N) out(L.li(q), y[v]);
     }
+    __syncthreads();
+}
+
+// v = sigma A x for every node, a Krylov vector of the step (sums as in held_sum_wide).
+template <typename T, int R>
+__device__ __forceinline__ void tail_power(const TLv<T>& L, int ln, const THeld<T, R>& h, const cplx<T>* x, cplx<T>* v) {
+    cplx<double> y{0.0, 0.0};
+    if (ln >= 0) y = h.template apply<true>(L, ln, x);
+    if (ln >= 0 && held_part() == 0) v[ln] = cast<T>(L.sigma * y);
+    __syncthreads();
+}
+template <typename T, int R>
+__device__ __forceinline__ void tail_power(const TLv<T>& L, int, const TBig<R>&, const cplx<T>* x, cplx<T>* v) {
+    tnodes(L, [&](int q) {
+        const cplx<T>* xq = x + L.li(q);
+        const cplx<T>* cp = L.coef + L.gi(q);
+        cplx<double> y{0.0, 0.0};
+#pragma unroll 1
+        for (int dy = -R; dy <= R; ++dy)
+#pragma unroll
+            for (int dx = -R; dx <= R; ++dx)
+                y = cfma(y, cast<double>(cp[(long long)((dy + R) * (2 * R + 1) + dx + R) * L.g.plane]),
+                         cast<double>(xq[dy * L.lp + dx]));
+        v[L.li(q)] = cast<T>(L.sigma * y);
+    });
     __syncthreads();
 }
 
@@ -229,7 +263,7 @@ __device__ __forceinline__ GmWeights<T> tail_weights(const TLv<T>& L, const cplx
     if (wave == 0) {
         const R sum = sum_rows(sh.part, wn, lane);
         GmWeights<T> w;
-        weights_of<T>(sum, L.sigma, 0.0, w);
+        weights_of<T>(sum, GmBasis{L.sigma, {0.0, 0.0, 0.0}, kPivotMin<T>}, w);
         if (lane == 0) sh.w = w;
     }
     __syncthreads();
@@ -248,15 +282,14 @@ __device__ __forceinline__ void tail_gmres(const TLv<T>& L, int ln, const H& h, 
     cplx<T>* v1 = L.s(1);
     cplx<T>* v2 = L.s(2);
     cplx<T>* v3 = L.s(3);
-    const T sg = T(L.sigma);
     if (!from_zero) {
         cplx<T>* r = L.s(0);
         tail_apply<false>(L, ln, h, u, [&](int l, cplx<T> y) { r[l] = f[l] - y; });
     }
     const cplx<T>* v0 = from_zero ? f : L.s(0);
-    tail_apply<false>(L, ln, h, v0, [&](int l, cplx<T> y) { v1[l] = sg * y; });
-    tail_apply<false>(L, ln, h, v1, [&](int l, cplx<T> y) { v2[l] = sg * y; });
-    tail_apply<false>(L, ln, h, v2, [&](int l, cplx<T> y) { v3[l] = sg * y; });
+    tail_power(L, ln, h, v0, v1);
+    tail_power(L, ln, h, v1, v2);
+    tail_power(L, ln, h, v2, v3);
     const GmWeights<T> w = tail_weights<H>(L, v0, v1, v2, v3, sh);
     tail_nodes<H>(L, [&](int l) {
         const cplx<T> a = v0[l], b = v1[l], c = v2[l], d = v3[l];

@@ -51,6 +51,29 @@ def gmres_step(A, u, f):
     return u + sum(g[j] * z[j] for j in range(3))
 
 
+def cycle(H, u, f, pre, post):
+    """u after one V(pre, post) cycle of the oracle's hierarchy H on A u = f."""
+    A = [Matrix(a) for a in H.A]
+    P, R = [Matrix(p) for p in H.P], [Matrix(r) for r in H.R]
+    coarsest = H.A[-1].toarray()
+
+    def level(l, u, f):
+        if l == H.levels - 1:
+            x = np.zeros_like(f)
+            for _ in range(4):  # FP64 solves refined
+                x = x + np.linalg.solve(coarsest, (f - A[l] @ x).astype(np.complex128))
+            return x
+        for _ in range(pre):
+            u = gmres_step(A[l], u, f)
+        fc = R[l] @ (f - A[l] @ u)
+        u = u + P[l] @ level(l + 1, np.zeros_like(fc), fc)
+        for _ in range(post):
+            u = gmres_step(A[l], u, f)
+        return u
+
+    return level(0, u, f)
+
+
 def amplification(A, f, u, shift):
     """sum |c_j| ||v_j|| / ||u|| for u = sum c_j v_j over v_j = (A - shift)^j f, j < 3: how far
     rounding of the v_j and c_j grows in u."""
