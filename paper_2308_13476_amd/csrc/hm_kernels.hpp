@@ -224,6 +224,9 @@ void launch_grad_k2(const LaunchCtx&, Grid g, double h, const double* k2, Vec<do
 constexpr int kMaxTailLevels = 8;
 constexpr int kTailGhost = 3;
 constexpr int kTailMaxCoarseNodes = 81;              // coarsest (n_c + 1)^2 of a tail
+constexpr int kTailThreads = 640;                    // threads of a tail workgroup
+constexpr int kTailNodesPerThread = 2;
+constexpr int kTailMaxNodes = kTailThreads * kTailNodesPerThread;  // (n + 1)^2 of its first level
 constexpr long long kTailMaxLdsBytes = 152 * 1024;   // dynamic LDS of one tail workgroup
 __host__ __device__ inline int tail_pitch(int n) { return n + 1 + 2 * kTailGhost; }
 __host__ __device__ inline int tail_planes(int q, int nlev) { return q + 1 < nlev ? 6 : 2; }

@@ -724,9 +724,9 @@ mg_status build_hierarchy(mg_ctx* c, const double* k2, hipStream_t s, hipEvent_t
 }
 
 // Levels of at most tail_n intervals (HELMG_TAIL_N, default 16) run in the
-// single-workgroup tail when all of them fit its LDS budget at the cycle's
-// precision and the coarsest grid is small enough for the explicit inverse;
-// HELMG_TAIL_N = 0 turns the tail off.
+// single-workgroup tail when its threads cover the nodes of the first, all of them
+// fit its LDS budget at the cycle's precision and the coarsest grid is small enough
+// for the explicit inverse; HELMG_TAIL_N = 0 turns the tail off.
 void pick_tail_levels(mg_ctx* c, int tail_n) {
     const int L = c->L;
     const int nc = c->n >> (L - 1);
@@ -736,7 +736,8 @@ void pick_tail_levels(mg_ctx* c, int tail_n) {
         c->tail_level[prec] = -1;
         if (tail_n <= 0 || !small_coarse) continue;
         for (int l = 1; l < L; ++l) {
-            if ((c->n >> l) > tail_n || L - l > kMaxTailLevels) continue;
+            const int m = (c->n >> l) + 1;
+            if (m - 1 > tail_n || m * m > kTailMaxNodes || L - l > kMaxTailLevels) continue;
             long long bytes = 0;
             for (int q = 0; q < L - l; ++q) bytes += tail_plane_values(c->n >> (l + q), q, L - l) * elem;
             if (bytes <= kTailMaxLdsBytes) {

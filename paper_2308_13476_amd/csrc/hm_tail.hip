@@ -21,8 +21,7 @@ namespace hm {
 namespace {
 
 // Ten wavefronts: two lanes for each of the 289 nodes of a 16-interval level.
-constexpr int kTailWaves = 10;
-constexpr int kTailThreads = 64 * kTailWaves;
+constexpr int kTailWaves = kTailThreads / 64;
 
 // One level of the tail: its stencil in global memory and its LDS planes.
 // LDS planes have a zero frame of kTailGhost nodes: node (i, j) sits at
@@ -137,7 +136,7 @@ template <typename H>
 struct TTag {
     using type = H;
 };
-constexpr int kBigNodes = 2;  // nodes per thread: (32 + 1)^2 nodes at most
+constexpr int kBigNodes = kTailNodesPerThread;
 
 // out(l, (A x)_q) for every node, l its LDS index (ln: that of the held node of
 // this lane, or -1), x a plane of the level. kInPlace: out may overwrite x, so
