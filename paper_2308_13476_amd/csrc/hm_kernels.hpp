@@ -2,9 +2,27 @@
 // Every launcher enqueues on ctx.stream and never synchronises.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <mutex>
 #include "hm_common.hpp"
 
 namespace hm {
+
+constexpr int kMaxDevices = 64;
+
+// Runs f the first time it is called for a device.
+class OncePerDevice {
+    std::mutex mu_;
+    bool done_[kMaxDevices] = {};
+
+public:
+    template <typename F>
+    void operator()(int device, F&& f) {
+        std::lock_guard<std::mutex> lock(mu_);
+        if (device < 0 || device >= kMaxDevices || done_[device]) return;
+        f();
+        done_[device] = true;
+    }
+};
 
 // Per-right-hand-side norms read by the host.
 struct RhsNorms {
@@ -265,10 +283,11 @@ struct TailArgs {
 // the range that FP32 residuals have.
 double gm_sigma(double h, int level);
 template <typename T> void launch_tail(const LaunchCtx&, const TailArgs<T>&);
-// Raise the dynamic-LDS limits of the tail and LU kernels (once per process; call
-// before the first launch, outside stream capture).
-void tail_init();
-void setup_init();
+// Raise the dynamic-LDS limits of the tail and LU kernels on the current device, which
+// is `device` (once per device; call before the first launch there, outside stream
+// capture).
+void tail_init(int device);
+void setup_init(int device);
 // inv = A^{-1} from the LU factor and pivots of launch_dense_lu.
 void launch_lu_inverse(hipStream_t, int N, const cplx<double>* lu, const int* piv, cplx<double>* inv);
 

@@ -32,7 +32,6 @@ thread_local std::string g_setup_error;
 // kept in g_scratch_ptr.
 constexpr size_t kStaticScratchBytes = size_t(64) << 20;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
-constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 void* g_scratch_ptr[kMaxDevices] = {};
 
@@ -1169,11 +1168,10 @@ mg_status mg_setup(const double* k2, int n, double h, double shift, int levels, 
         c->tail_n = tail_n;
         pick_tail_levels(c, tail_n);
     }
-    tail_init();
-    setup_init();
     {
         // the device and, once per device, the address of the static scratch
         // of mg_residual_noalloc (looked up here, at set-up, with the device current)
+        // and the kernels' launch limits
         void* scr = nullptr;
         hipError_t e = hipGetDevice(&c->device);
         if (e == hipSuccess) e = static_scratch(c->device, &scr);
@@ -1182,6 +1180,8 @@ mg_status mg_setup(const double* k2, int n, double h, double shift, int levels, 
             delete c;
             return MG_E_HIP;
         }
+        tail_init(c->device);
+        setup_init(c->device);
     }
     carve(c, c->ws, n, L, transfer, max_batch, has32);
     hipStream_t s = static_cast<hipStream_t>(stream);

@@ -664,13 +664,12 @@ void launch_galerkin(hipStream_t s, int fine_level, Grid fine, int fine_radius, 
                        int(transfer == 0), coarse_coef);
 }
 
-void setup_init() {
-    static const bool done = [] {
+void setup_init(int device) {
+    static OncePerDevice once;
+    once(device, [] {
         (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_lu<true>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, int(kLuLdsBytes));
-        return true;
-    }();
-    (void)done;
+    });
 }
 
 void launch_cast_coef(hipStream_t s, const cplx<double>* src, cplx<float>* dst, long long count) {

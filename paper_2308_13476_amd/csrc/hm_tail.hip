@@ -530,8 +530,9 @@ static void with_tail_kernel(int r0, F&& f) {
     else f(&k_tail<T, 3, 3>);
 }
 
-void tail_init() {
-    static const bool done = [] {
+void tail_init(int device) {
+    static OncePerDevice once;
+    once(device, [] {
         for (int r = 1; r <= 3; ++r) {
             auto raise = [](auto kern) {
                 (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -540,9 +541,7 @@ void tail_init() {
             with_tail_kernel<double>(r, raise);
             with_tail_kernel<float>(r, raise);
         }
-        return true;
-    }();
-    (void)done;
+    });
 }
 
 template <typename T>
