@@ -71,10 +71,12 @@ constexpr int kBX = 64;
 constexpr int kBY = 4;      // short blocks (register-heavy stencils, small grids)
 constexpr int kMaxBY = 16;  // tall blocks (light kernels on large grids)
 
-// A level kernel launches at most kMaxPartialBlocks blocks per right-hand
-// side; reductions keep up to 8 partial sums per block in each of two
-// regions. Consumers reduce the partials themselves up to the runtime block
-// cap; above it a one-block pass pre-reduces them first.
+// A level kernel launches at most kMaxPartialBlocks blocks per right-hand side. Its
+// partial sums go to one of two regions of kPartStride doubles per right-hand side: up
+// to eight for each of that many blocks, or the Gram sums of a GMRES(3) step, sixteen
+// (FP32) or thirty-two per block, of at most 4096 or 2048 blocks. Consumers reduce the
+// partials themselves up to the runtime block cap; above it a one-block pass
+// pre-reduces them first.
 constexpr int kMaxPartialBlocks = 8192;
 constexpr long long kPartStride = (long long)kMaxPartialBlocks * 8;  // doubles per (region, right-hand side)
 
