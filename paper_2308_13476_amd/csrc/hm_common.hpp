@@ -14,8 +14,6 @@ struct alignas(2 * sizeof(T)) cplx {
 };
 
 template <typename T>
-__host__ __device__ __forceinline__ cplx<T> mk(T r, T i) { return cplx<T>{r, i}; }
-template <typename T>
 __device__ __forceinline__ cplx<T> operator+(cplx<T> a, cplx<T> b) { return {a.re + b.re, a.im + b.im}; }
 template <typename T>
 __device__ __forceinline__ cplx<T> operator-(cplx<T> a, cplx<T> b) { return {a.re - b.re, a.im - b.im}; }
@@ -32,8 +30,6 @@ __device__ __forceinline__ cplx<T> cfma(cplx<T> a, cplx<T> b, cplx<T> c) {
 }
 template <typename T>
 __device__ __forceinline__ cplx<T> conj(cplx<T> a) { return {a.re, -a.im}; }
-template <typename T>
-__device__ __forceinline__ T norm2(cplx<T> a) { return a.re * a.re + a.im * a.im; }
 // a / b
 template <typename T>
 __device__ __forceinline__ cplx<T> cdiv(cplx<T> a, cplx<T> b) {

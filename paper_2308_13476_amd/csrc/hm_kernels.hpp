@@ -321,7 +321,7 @@ void launch_galerkin(hipStream_t, int fine_level, Grid fine, int fine_radius, co
 void launch_cast_coef(hipStream_t, const cplx<double>* src, cplx<float>* dst, long long count);
 // Dense coarsest matrix [N][N] (N = (n_c+1)^2) from stencil planes, then LU with partial pivoting.
 void launch_dense_lu(hipStream_t, Grid g, int radius, const cplx<double>* coef, cplx<double>* dense, int* piv);
-// u = A^{-1} f on the coarsest grid with the stored LU (FP64 arithmetic).
+// u = A^{-1} f on the coarsest grid with the explicit inverse (FP64 arithmetic).
 template <typename T>
 void launch_coarse_solve(const LaunchCtx&, Grid g, const cplx<double>* inv, Vec<T> f, Vec<T> u);
 // Stencil planes -> caller's dense [(2r+1)^2][n_l+1][n_l+1] complex128.

@@ -295,7 +295,7 @@ __device__ __forceinline__ void product_stages(const ProductOp<T, kBez>& op, con
     });
 }
 
-template <typename Op, typename T, bool kXcd = false, typename PGet, typename F>
+template <typename Op, typename T, typename PGet, typename F>
 __device__ __forceinline__ void apply_from_tile(const Op& op, int rpt, const Tile<op_radius<Op>::value>& tl,
                                                 cplx<T>* lds, PGet&& pget, F&& f);
 
@@ -317,11 +317,10 @@ __device__ __forceinline__ void for_nodes_applied_pre(const Op& op, int rpt, XLo
 
 // The second half of for_nodes_applied_pre: x of the block tile plus halo is
 // in LDS (after a barrier); runs f(i, j, p, pget(p), x at p, A x at p).
-template <typename Op, typename T, bool kXcd, typename PGet, typename F>
+template <typename Op, typename T, typename PGet, typename F>
 __device__ __forceinline__ void apply_from_tile(const Op& op, int rpt, const Tile<op_radius<Op>::value>& tl,
                                                 cplx<T>* lds, PGet&& pget, F&& f) {
     if constexpr (is_product<Op>::value) {
-        static_assert(!kXcd, "the XCD tile map is used by level-0 passes only");
         product_stages(op, tl, lds, pget, f);
     } else if constexpr (std::is_same<Op, FineOp<T>>::value) {
         // tiles whose nodes all lie strictly inside the grid skip the boundary
@@ -333,7 +332,7 @@ __device__ __forceinline__ void apply_from_tile(const Op& op, int rpt, const Til
         decltype(pget(0LL)) pv[NB];
         T kk[NB];
         auto rows = [&](auto inner) {
-            for_nodes_batched<NB, kXcd>(
+            for_nodes_batched<NB>(
                 op.g, rpt,
                 [&](int u, long long p) {
                     pv[u] = pget(p);
@@ -357,7 +356,7 @@ __device__ __forceinline__ void apply_from_tile(const Op& op, int rpt, const Til
         constexpr int NB = is_stencil<Op>::value ? (sizeof(T) == 4 ? 2 : 1) : (sizeof(T) == 4 ? 8 : 4);
         decltype(pget(0LL)) pv[NB];
         typename OpPre<Op>::type ov[NB];
-        for_nodes_batched<NB, kXcd>(
+        for_nodes_batched<NB>(
             op.g, rpt,
             [&](int u, long long p) {
                 pv[u] = pget(p);
