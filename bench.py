@@ -55,9 +55,21 @@ CLASS1_FP32_K2_BYTES = 4.0
 # algorithmic bytes. Valid only for the kernel sources they were measured on:
 # the hash below is of the files in TRAFFIC_SOURCES, and a different hash
 # reports traffic as null.
-TRAFFIC_SOURCES = ["paper_2308_13476_amd/csrc/hm_level.hip", "paper_2308_13476_amd/csrc/hm_ops.hpp",
-                   "paper_2308_13476_amd/csrc/hm_common.hpp", "paper_2308_13476_amd/csrc/hm_kernels.hpp"]
-MEASURED_TRAFFIC = None
+TRAFFIC_SOURCES = ["paper_2308_13476_amd/csrc/" + name
+                   for name in ("hm_gmres.hpp", "hm_gram.hpp", "hm_gmres_f32.hip", "hm_gmres_f64.hip", "hm_level.hpp",
+                                "hm_ops.hpp", "hm_common.hpp", "hm_kernels.hpp")]
+MEASURED_TRAFFIC = {
+    "sources_sha256": "516e3c3257dad6db863c694ab4af441fc4466ed0e206a82e836d38058b979bbc",
+    # k_gm_march<float, 4> at n = 1024 (headline workload)
+    "mp2a": {"fetch_bytes": 13992803, "write_bytes": 21173453,
+             "profile": "profiles/fp32_cycle_level0_n1024_hbm_traffic.md"},
+    # k_gm_march<double, 2> at n = 2048 (working set beyond the Infinity Cache)
+    "beyond_cache": {"fetch_bytes": 117523203, "write_bytes": 168881152,
+                     "profile": "profiles/fp64_level0_n2048_hbm_traffic.md"},
+    # k_gm_march<float, 4>, 64 right-hand sides on n = 512
+    "batch64": {"fetch_bytes": 188760785, "write_bytes": 337536717,
+                "profile": "profiles/batch64_n512_hbm_traffic.md"},
+}
 
 
 def measured_traffic(which):

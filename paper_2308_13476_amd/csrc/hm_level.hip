@@ -1,5 +1,5 @@
 // Level kernels of the multigrid cycle: operator apply, residual, weighted
-// Jacobi, transfers, GMRES(3) passes, norms, FP32 refinement, adjoint gradient.
+// Jacobi, transfers, norms, FP32 refinement, adjoint gradient.
 #include <cmath>
 
 #include "hm_level.hpp"
