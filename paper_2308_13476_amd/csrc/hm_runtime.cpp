@@ -724,8 +724,8 @@ mg_status build_hierarchy(mg_ctx* c, const double* k2, hipStream_t s, hipEvent_t
 
 // Levels of at most tail_n intervals (HELMG_TAIL_N, default 16) run in the
 // single-workgroup tail when its threads cover the nodes of the first, all of them
-// fit its LDS budget at the cycle's precision and the coarsest grid is small enough
-// for the explicit inverse; HELMG_TAIL_N = 0 turns the tail off.
+// fit its LDS budget at the cycle's precision and the coarsest grid has at most
+// kTailMaxCoarseNodes nodes; HELMG_TAIL_N = 0 turns the tail off.
 void pick_tail_levels(mg_ctx* c, int tail_n) {
     const int L = c->L;
     const int nc = c->n >> (L - 1);
